@@ -458,6 +458,11 @@ struct NbrCells {
     sy = __builtin_fmaf((float)((v >> 8) & 0xffu), s, -s);
     sz = __builtin_fmaf((float)((v >> 16) & 0xffu), s, -s);
   }
+  // whether q is one of the chunk's own m cells, and not a periodic image of
+  // one (the cells around m > n_c - 2 cells hold images of them)
+  __device__ __forceinline__ bool own(int q, int m) const {
+    return (d[q] >> 8) == 0x0101 && (d[q] & 0xff) <= m && (d[q] & 0xff) != 0;
+  }
   __device__ __forceinline__ void offsets(int q, int& dx, int& dy, int& dz) const {
     const int v = d[q];
     dx = (v & 0xff) - 1;
@@ -1854,7 +1859,8 @@ __global__ __launch_bounds__(TI* K, kForceBlocks<TI * K>) void k_force(Src, Cell
           cs4[sl] = make_float4(1.0f / (gk * hj),
                                 (ph.gradh ? d4[r].y : 1.0f) * d4[r].z / (d4[r].x * d4[r].x),
                                 d4[r].w, d4[r].x);
-          if (real && jj[r] >= c0 && jj[r] < c1) selfpos[jj[r] - c0] = (nbatch << 16) | sl;
+          if (real && jj[r] >= c0 && jj[r] < c1 && T.own(qq[r], m))
+            selfpos[jj[r] - c0] = (nbatch << 16) | sl;
         }
       }
     };

@@ -50,7 +50,7 @@ def _set(orc, wide, thin=1):
 @pytest.fixture(scope="module")
 def sets(orc):
     out = {}
-    for name, wide, thin in (("mixed", False, 1), ("wide", True, 1)):
+    for name, wide, thin in (("mixed", False, 1), ("wide", True, 1), ("sparse", True, 24)):
         ps = _set(orc, wide, thin)
         # without grad-h factors: on a few random neighbours those are 1 / (a
         # difference near zero), which no FP32 bar holds for
@@ -58,11 +58,12 @@ def sets(orc):
     return out
 
 
-@pytest.mark.parametrize("which", ["mixed", "wide"])
+@pytest.mark.parametrize("which", ["mixed", "wide", "sparse"])
 @pytest.mark.parametrize("ti,k", TILES)
 def test_chunk_and_list_sizes(sph, orc, sets, ti, k, which):
     ps, d, f = sets[which]
-    kw = {"mixed": {}, "wide": {"sub_bits": 1, "sched": "grid"}}[which]
+    kw = {"mixed": {}, "wide": {"sub_bits": 1, "sched": "grid"},
+          "sparse": {"sched": "dynamic", "max_cells": 4}}[which]
     pipe = run_gpu(ps, N_C, "f32", til=sph.tile(ti, k), prm=sph.params(gradh=False), **kw)
     assert pipe.status() == 0
     got = gpu_fields(pipe)
