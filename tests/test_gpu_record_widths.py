@@ -1,0 +1,103 @@
+"""Conversion and writeback of records of other widths than the two of
+inputs: fields in any order and type, a 4-byte field beside one that is not
+the library's, absent fields, the widest staged record and one beyond it;
+one slot, a tile less one, a tile, one more. Every stored value is exact, and
+a byte that belongs to no field written keeps its value."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+F, D, I = "<f4", "<f8", "<i4"
+IN = [("x", D, 3), ("v", None, 3), ("m", None, 1), ("h", None, 1), ("u", None, 1)]
+OUT = [("rho", None, 1), ("wcount", None, 1), ("rho_dh", None, 1), ("f", None, 1),
+       ("P", None, 1), ("c", None, 1), ("nngb", I, 1), ("a", None, 3), ("du", None, 1),
+       ("vsig", None, 1), ("nforce", I, 1), ("cell", I, 1)]
+SOA = {"rho": "RHO", "wcount": "WCOUNT", "rho_dh": "RHO_DH", "f": "F", "P": "P", "c": "C",
+       "nngb": "NNGB", "du": "DU", "vsig": "VSIG", "nforce": "NFORCE"}
+
+
+def _dtype(stride, order, kinds, absent=()):
+    """A record of `stride` bytes: fields in a random order, each FP32 or FP64
+    (kinds), 8-byte ones aligned, with unused 4-byte holes between some."""
+    rng = np.random.default_rng(order)
+    names, formats, offsets, at = [], [], [], 0
+    for name, t, k in [(IN + OUT)[i] for i in rng.permutation(len(IN + OUT))]:
+        if name in absent:
+            continue
+        t = t or (kinds if kinds in (F, D) else (F, D)[rng.integers(2)])
+        at += 4 * (rng.integers(3) == 0 and kinds != D)
+        at = (at + 7) // 8 * 8 if t == D else at
+        names.append(name)
+        formats.append((t, (k,)) if k > 1 else t)
+        offsets.append(at)
+        at += k * np.dtype(t).itemsize
+    assert at <= stride, at
+    return np.dtype({"names": names, "formats": formats, "offsets": offsets, "itemsize": stride})
+
+
+LAYOUTS = [_dtype(136, 1, F), _dtype(152, 2, F), _dtype(208, 3, D), _dtype(192, 4, "mixed"),
+           _dtype(248, 5, "mixed"), _dtype(256, 6, "mixed"),
+           _dtype(200, 7, "mixed", absent=("wcount", "f", "nforce", "cell"))]
+
+
+@pytest.fixture(scope="module")
+def sph():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2512_05516_amd import sphmi
+    sphmi.lib()
+    return sphmi
+
+
+@pytest.mark.parametrize("lay", range(len(LAYOUTS)))
+@pytest.mark.parametrize("n", [1, 255, 256, 257, 1300])
+def test_record_widths(sph, n, lay):
+    import torch
+    from paper_2512_05516_amd.pipeline import Pipeline
+    dt = LAYOUTS[lay]
+    rng = np.random.default_rng(100 * n + lay)
+    raw = rng.integers(0, 256, n * dt.itemsize, dtype=np.uint8)
+    rec = raw.view(dt)
+    rec["x"] = rng.uniform(0, 1, (n, 3))
+    for k in ("v", "m", "h", "u"):
+        rec[k] = rng.uniform(0.01, 0.02, rec[k].shape)
+    pipe = Pipeline(rec, 3)
+    pipe.bin()
+    pipe.convert("full")
+    torch.cuda.synchronize()
+    perm = pipe.cells.perm[:n].cpu().numpy()
+    f32 = lambda a: np.asarray(a, np.float32)
+    for c, ax in enumerate("XYZ"):
+        assert np.array_equal(pipe.soa["X_" + ax].cpu().numpy(), rec["x"][perm, c])
+        assert np.array_equal(pipe.soa["V_" + ax].cpu().numpy(), f32(rec["v"][perm, c]))
+        assert np.array_equal(pipe.soa["VQ_" + ax].cpu().numpy(), f32(rec["v"][perm, c]))
+    for k, s in (("m", "M"), ("h", "H"), ("u", "U"), ("u", "UK")):
+        assert np.array_equal(pipe.soa[s].cpu().numpy(), f32(rec[k][perm])), k
+
+    new = {}
+    for s in list(SOA.values()) + ["A_X", "A_Y", "A_Z", "V_X", "V_Y", "V_Z", "UK", "X_X", "X_Y",
+                                   "X_Z"]:
+        v = (rng.integers(0, 1000, n) if s in ("NNGB", "NFORCE") else rng.normal(0, 1, n))
+        new[s] = torch.from_numpy(v).to(pipe.soa[s].dtype)
+        pipe.soa[s].copy_(new[s])
+    groups = {"kick": ("x", "v", "u"), "density": ("rho", "wcount", "rho_dh", "f", "P", "c", "nngb"),
+              "force": ("a", "du", "vsig", "nforce")}
+    groups["full"] = sum(groups.values(), ()) + ("cell",)
+    for view, fields in groups.items():
+        pipe.aos.copy_(torch.from_numpy(raw.copy()).view_as(pipe.aos))
+        pipe.writeback(view)
+        buf = raw.copy()
+        want = buf.view(dt)
+        for k in fields:
+            if k not in dt.names:
+                continue
+            if k in ("x", "v", "a"):
+                for c, ax in enumerate("XYZ"):
+                    want[k][perm, c] = new[f"{k.upper()}_{ax}"].numpy()
+            elif k == "cell":
+                want[k][perm] = pipe.cells.cell[:n].cpu().numpy()
+            else:
+                want[k][perm] = new["UK" if k == "u" else SOA[k]].numpy()
+        assert np.array_equal(pipe.aos.cpu().numpy(), buf), view
