@@ -10,9 +10,17 @@
 // outputs, so no result depends on the split, the order or the schedule.
 //
 // Buffer layout: [0, kWorkHeader) queue counters[8] and meta (item count,
-// range boundaries[9]); then the item offsets [C + 1] and the cost prefix
-// [C + 1] of the cells in brick order, one set of scan partials, and the
-// items (int2: cell, first slot).
+// range boundaries[9]); then the prefixes of the items and of the costs of
+// the cells in brick order ([C + 1] each, see k_wl_count) and the items (int2:
+// cell, first slot), after a gap of scan_partials_count(C + 1) words that is
+// part of the buffer's size.
+//
+// Two launches: the lists are short (a few us of work), so what a build costs
+// is its launches. With separate scans of items and costs and a kernel for the
+// boundaries, nine launches, it took 37 us for 4096 cells and 59 us for
+// 287496; now 13 and 30.
+#include <algorithm>
+
 #include "sph_device.h"
 
 namespace sph {
@@ -25,9 +33,8 @@ constexpr int kNbCap = 27 * 64;  // neighbour-count cap of the cost estimate
 inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
 struct WlLayout {
-  int32_t* pos;       // [C + 1] first item of each cell (brick order)
-  int32_t* cost;      // [C + 1] exclusive prefix of the cell costs (brick order)
-  int32_t* partials;
+  int32_t* pos;       // [C + 1] item prefixes of the cells (brick order)
+  int32_t* cost;      // [C + 1] cost prefixes of the cells (brick order)
   int2* items;
 };
 
@@ -40,7 +47,6 @@ WlLayout wl_layout(void* buf, int C) {
   p += al256(sizeof(int32_t) * ((size_t)C + 1));
   L.cost = reinterpret_cast<int32_t*>(p);
   p += al256(sizeof(int32_t) * ((size_t)C + 1));
-  L.partials = reinterpret_cast<int32_t*>(p);
   p += al256(sizeof(int32_t) * scan_partials_count(C + 1));
   L.items = reinterpret_cast<int2*>(p);
   return L;
@@ -89,109 +95,188 @@ __device__ __forceinline__ int merge_group(const int32_t* __restrict__ start, in
   return 1;
 }
 
+// Cells of a block: `rounds` times kThreads, so that at most kMaxBlocks blocks
+// hold all cells and every block can add up the totals of those before it.
+constexpr int kMaxBlocks = 4 * kThreads;
+int wl_rounds(int C) { return std::max(cdiv(C, kThreads * kMaxBlocks), 1); }
+
+// items << 32 | cost of a range of cells: both sums stay below 2^31
+__device__ __forceinline__ uint64_t pair64(int items, int cost) {
+  return (uint64_t)(uint32_t)items << 32 | (uint32_t)cost;
+}
+__device__ __forceinline__ int items_of(uint64_t v) { return (int)(v >> 32); }
+__device__ __forceinline__ int cost_of(uint64_t v) { return (int)(uint32_t)v; }
+
+// Exclusive prefix of v over the block; `total`: the block's sum
+__device__ __forceinline__ uint64_t block_prefix(uint64_t v, uint64_t& total, uint64_t* lds) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint64_t inc = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint64_t t = __shfl_up(inc, o);
+    inc += lane >= o ? t : 0;
+  }
+  if (lane == 63) lds[wave] = inc;
+  __syncthreads();
+  uint64_t pre = inc - v;
+  total = 0;
+#pragma unroll
+  for (int w = 0; w < kThreads / 64; ++w) {
+    pre += w < wave ? lds[w] : 0;
+    total += lds[w];
+  }
+  __syncthreads();
+  return pre;
+}
+
+// Particles in the cells x - 1 .. x + 1 of a row (the row's first cell: row)
+__device__ __forceinline__ int row_count(const int32_t* __restrict__ start, int n_c, int n,
+                                         int row, int cx) {
+  auto slot = [&](int c) { return min(max(start[c], 0), n); };
+  if (cx > 0 && cx + 1 < n_c) return max(slot(row + cx + 2) - slot(row + cx - 1), 0);
+  int k = 0;
+  for (int dx = -1; dx <= 1; ++dx)
+    k += cell_count(start, row + (cx + dx + n_c) % n_c, n);
+  return k;
+}
+
 // Items per cell and the cell's cost estimate, clamped so that the sum over
-// all cells fits in int32.
+// all cells fits in int32, as exclusive prefixes within the block's cells. The
+// first cell of a block, whose prefix is zero, holds the block's total instead.
 __global__ __launch_bounds__(kThreads) void k_wl_count(const int32_t* __restrict__ start, int n_c,
-                                                        int n, int ti, int cost_cap,
+                                                        int n, int ti, int cost_cap, int rounds,
                                                         const uint8_t* __restrict__ active,
                                                         int occ_lo, int occ_hi, int merge,
                                                         int32_t* __restrict__ pos,
                                                         int32_t* __restrict__ cost,
                                                         const int32_t* gate) {
+  __shared__ uint64_t lds[kThreads / 64];
   if (gate && *gate == 0) return;             // the cell list was kept: so is this list
   const int C = n_c * n_c * n_c;
-  const int j = blockIdx.x * kThreads + threadIdx.x;   // position in brick order
-  if (j > C) return;
-  if (j == C) {
-    pos[C] = 0;
-    cost[C] = 0;
-    return;
-  }
-  const int c = brick_cell(j, n_c);
-  int cnt = cell_count(start, c, n);
-  if (cnt < occ_lo || cnt >= occ_hi) cnt = 0;   // only cells of this occupancy class
-  if (active && cnt > 0) {   // only cells that hold an active slot
-    const int a = min(max(start[c], 0), n);
-    bool any = false;
-    for (int k = a; k < a + cnt && !any; ++k) any = active[k] != 0;
-    if (!any) cnt = 0;
-  }
-  if (merge > 1 && cnt > 0 && cnt <= ti) {
-    const int m = merge_group(start, n, n_c, ti, merge, occ_lo, occ_hi, c);
-    pos[j] = m > 0 ? 1 : 0;          // the group's first cell holds its one item
-  } else {
-    pos[j] = (cnt + ti - 1) / ti;
-  }
-  int cx, cy, cz;
-  cell_coords(c, n_c, cx, cy, cz);
-  int64_t nb = 0;
-  for (int dz = -1; dz <= 1; ++dz) {
-    const int z = (cz + dz + n_c) % n_c;
-    for (int dy = -1; dy <= 1; ++dy) {
-      const int y = (cy + dy + n_c) % n_c;
-      for (int dx = -1; dx <= 1; ++dx) {
-        const int x = (cx + dx + n_c) % n_c;
-        nb += cell_count(start, x + n_c * (y + n_c * z), n);
+  const int j0 = blockIdx.x * (rounds * kThreads);
+  uint64_t carry = 0;
+  for (int r = 0; r < rounds; ++r) {
+    const int j = j0 + r * kThreads + threadIdx.x;   // position in brick order
+    int items = 0, units = 0;
+    if (j < C) {
+      const int c = brick_cell(j, n_c);
+      int cnt = cell_count(start, c, n);
+      if (cnt < occ_lo || cnt >= occ_hi) cnt = 0;   // only cells of this occupancy class
+      if (active && cnt > 0) {   // only cells that hold an active slot
+        const int a = min(max(start[c], 0), n);
+        bool any = false;
+        for (int k = a; k < a + cnt && !any; k += 8) {   // eight loads in flight
+#pragma unroll
+          for (int u = 0; u < 8; ++u) any |= active[min(k + u, a + cnt - 1)] != 0;
+        }
+        if (!any) cnt = 0;
+      }
+      if (merge > 1 && cnt > 0 && cnt <= ti) {
+        const int m = merge_group(start, n, n_c, ti, merge, occ_lo, occ_hi, c);
+        items = m > 0 ? 1 : 0;         // the group's first cell holds its one item
+      } else {
+        items = (cnt + ti - 1) / ti;
+      }
+      if (cnt > 0) {
+        int cx, cy, cz;
+        cell_coords(c, n_c, cx, cy, cz);
+        int64_t nb = 0;
+#pragma unroll
+        for (int q = 0; q < 9; ++q) {
+          const int y = (cy + q % 3 - 1 + n_c) % n_c, z = (cz + q / 3 - 1 + n_c) % n_c;
+          nb += row_count(start, n_c, n, n_c * (y + n_c * z), cx);
+        }
+        // a chunk stages about the particles within a support radius of it; with
+        // h following the density that is a bounded number even next to crowded
+        // cells, so the neighbour count is capped at that of a 64-per-cell lattice
+        const int64_t raw = (int64_t)cnt * min(nb, (int64_t)kNbCap);
+        const int64_t u = (raw + (1 << kCostShift) - 1) >> kCostShift;
+        units = (int)min(u, (int64_t)cost_cap);
       }
     }
+    uint64_t total;
+    const uint64_t pre = carry + block_prefix(pair64(items, units), total, lds);
+    carry += total;
+    if (j < C && j != j0) {
+      pos[j] = items_of(pre);
+      cost[j] = cost_of(pre);
+    }
   }
-  // a chunk stages about the particles within a support radius of it; with
-  // h following the density that is a bounded number even next to crowded
-  // cells, so the neighbour count is capped at that of a 64-per-cell lattice
-  const int64_t raw = (int64_t)cnt * min(nb, (int64_t)kNbCap);
-  const int64_t units = (raw + (1 << kCostShift) - 1) >> kCostShift;
-  cost[j] = (int32_t)min(units, (int64_t)cost_cap);
+  if (threadIdx.x == 0) {
+    pos[j0] = items_of(carry);
+    cost[j0] = cost_of(carry);
+  }
 }
 
+// Writes the items, and the range boundaries: range q starts at the first item
+// of the first cell (in brick order) whose cost prefix reaches q/8 of the
+// total, so the cell before it writes the boundary.
 __global__ __launch_bounds__(kThreads) void k_wl_fill(const int32_t* __restrict__ start, int n_c,
-                                                       int n, int ti, int capacity, int merge,
-                                                       int occ_lo, int occ_hi,
+                                                       int n, int ti, int capacity, int rounds,
+                                                       int merge, int occ_lo, int occ_hi,
                                                        const int32_t* __restrict__ pos,
+                                                       const int32_t* __restrict__ cost,
                                                        int2* __restrict__ items,
+                                                       int32_t* __restrict__ counters,
+                                                       int32_t* __restrict__ meta,
                                                        const int32_t* gate) {
+  __shared__ uint64_t lds[kThreads / 64];
   if (gate && *gate == 0) return;
   const int C = n_c * n_c * n_c;
-  const int j = blockIdx.x * kThreads + threadIdx.x;   // position in brick order
-  if (j >= C) return;
-  const int c = brick_cell(j, n_c);
-  const int a = min(max(start[c], 0), n), b = min(max(start[c + 1], a), n);
-  int o = pos[j];
-  const int end = min(pos[j + 1], capacity);   // this cell's items (none if filtered out)
-  if (merge > 1 && o < end && b - a <= ti) {   // one item: the cell or its merged group
-    const int m = max(merge_group(start, n, n_c, ti, merge, occ_lo, occ_hi, c), 1);
-    items[o] = make_int2(c | ((m - 1) << kMergeShift), a);
-    return;
-  }
-  for (int f = a; f < b && o < end; f += ti, ++o) items[o] = make_int2(c, f);
-}
-
-// Range boundaries: range q starts at the first item of the first cell (in
-// brick order) whose cost prefix reaches q/8 of the total.
-__global__ void k_wl_meta(const int32_t* __restrict__ pos, const int32_t* __restrict__ cost,
-                          int C, int capacity, int32_t* __restrict__ counters,
-                          int32_t* __restrict__ meta, const int32_t* gate) {
-  if (gate && *gate == 0) return;
-  const int q = threadIdx.x;
-  const int total = min(pos[C], capacity);
-  if (q == 0) meta[0] = total;
-  if (q > kQueues) return;
-  int b;
-  if (q == 0) {
-    b = 0;
-  } else if (q == kQueues) {
-    b = total;
-  } else {
-    const int64_t target = ((int64_t)cost[C] * q + kQueues - 1) / kQueues;
-    int lo = 0, hi = C;   // smallest c with cost[c] >= target
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      if (cost[mid] >= target) hi = mid;
-      else lo = mid + 1;
+  const int span = rounds * kThreads, j0 = blockIdx.x * span;
+  // totals of the blocks: those before this one, and all
+  uint64_t before = 0, sum = 0;
+#pragma unroll
+  for (int i = 0; i < kMaxBlocks / kThreads; ++i) {
+    const int b = i * kThreads + threadIdx.x;
+    if (b < (int)gridDim.x) {
+      const uint64_t v = pair64(pos[b * span], cost[b * span]);
+      sum += v;
+      before += b < (int)blockIdx.x ? v : 0;
     }
-    b = min(pos[lo], total);
   }
-  meta[1 + q] = b;
-  if (q < kQueues) counters[q] = b;
+  uint64_t base, all;
+  block_prefix(before, base, lds);
+  block_prefix(sum, all, lds);
+  const int total = min(items_of(all), capacity);
+  const int64_t cost_all = cost_of(all);
+  if (blockIdx.x == 0 && threadIdx.x <= kQueues) {
+    const int q = threadIdx.x;
+    if (q == 0) meta[0] = total;
+    if (q == 0 || q == kQueues || cost_all == 0) {
+      meta[1 + q] = q == kQueues ? total : 0;
+      if (q < kQueues) counters[q] = 0;
+    }
+  }
+  for (int r = 0; r < rounds; ++r) {
+    const int j = j0 + r * kThreads + threadIdx.x;   // position in brick order
+    if (j >= C) return;
+    const int je = min(j0 + span, C);
+    const int lp = j == j0 ? 0 : pos[j], lc = j == j0 ? 0 : cost[j];
+    const int np = j + 1 < je ? pos[j + 1] : pos[j0], nc = j + 1 < je ? cost[j + 1] : cost[j0];
+    int o = items_of(base) + lp;
+    const int next = items_of(base) + np;
+    const int64_t c0 = (int64_t)cost_of(base) + lc, c1 = (int64_t)cost_of(base) + nc;
+    if (c1 > c0) {
+      for (int q = 1; q < kQueues; ++q) {
+        const int64_t target = (cost_all * q + kQueues - 1) / kQueues;
+        if (c0 < target && target <= c1) {
+          meta[1 + q] = min(next, total);
+          counters[q] = min(next, total);
+        }
+      }
+    }
+    const int end = min(next, capacity);   // this cell's items (none if filtered out)
+    if (o >= end) continue;
+    const int c = brick_cell(j, n_c);
+    const int a = min(max(start[c], 0), n), b = min(max(start[c + 1], a), n);
+    if (merge > 1 && b - a <= ti) {   // one item: the cell or its merged group
+      const int m = max(merge_group(start, n, n_c, ti, merge, occ_lo, occ_hi, c), 1);
+      items[o] = make_int2(c | ((m - 1) << kMergeShift), a);
+      continue;
+    }
+    for (int f = a; f < b && o < end; f += ti, ++o) items[o] = make_int2(c, f);
+  }
 }
 
 }  // namespace
@@ -227,16 +312,12 @@ hipError_t launch_worklist_range(const CellsDev& c, const WorkDev& w, const uint
   const int cost_cap = (int)((((int64_t)1 << 31) - 1) / ((int64_t)C + 1));
   // merged items only for plain lists (the h iteration's lists filter cells)
   const int merge = active ? 1 : w.merge;
-  k_wl_count<<<cdiv(C + 1, kThreads), kThreads, 0, s>>>(c.start, c.n_c, c.n, w.ti, cost_cap,
-                                                         active, occ_lo, occ_hi, merge, L.pos,
-                                                         L.cost, gate);
-  hipError_t e = scan_i32(L.pos, C + 1, L.partials, s, gate);
-  if (e != hipSuccess) return e;
-  e = scan_i32(L.cost, C + 1, L.partials, s, gate);
-  if (e != hipSuccess) return e;
-  k_wl_fill<<<cdiv(C, kThreads), kThreads, 0, s>>>(c.start, c.n_c, c.n, w.ti, w.capacity, merge,
-                                                    occ_lo, occ_hi, L.pos, w.items, gate);
-  k_wl_meta<<<1, 64, 0, s>>>(L.pos, L.cost, C, w.capacity, w.counters, w.meta, gate);
+  const int rounds = wl_rounds(C), blocks = cdiv(C, rounds * kThreads);
+  k_wl_count<<<blocks, kThreads, 0, s>>>(c.start, c.n_c, c.n, w.ti, cost_cap, rounds, active,
+                                         occ_lo, occ_hi, merge, L.pos, L.cost, gate);
+  k_wl_fill<<<blocks, kThreads, 0, s>>>(c.start, c.n_c, c.n, w.ti, w.capacity, rounds, merge,
+                                        occ_lo, occ_hi, L.pos, L.cost, w.items, w.counters,
+                                        w.meta, gate);
   return hipGetLastError();
 }
 
