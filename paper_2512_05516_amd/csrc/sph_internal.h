@@ -82,12 +82,6 @@ hipError_t launch_bin(const void* aos, const AosLayout& L, const CellsDev& c, in
                       int32_t* perm, int32_t* cell, int32_t* sub_start, float* hmax, void* ws,
                       hipStream_t s);
 
-// exclusive scan of int32 in place; partials: scan_partials_count(len) ints;
-// with gate non-null the kernels do nothing when *gate == 0
-size_t scan_partials_count(int len);
-hipError_t scan_i32(int32_t* data, int len, int32_t* partials, hipStream_t s,
-                    const int32_t* gate = nullptr);
-
 size_t worklist_bytes(int n, int n_c, int ti);
 int worklist_capacity(int n, int n_c, int ti);
 hipError_t launch_worklist(const CellsDev& c, const WorkDev& w, hipStream_t s);
