@@ -40,6 +40,12 @@ static_assert(sizeof(sph_task_done) == 48, "sph_task_done layout");
 constexpr size_t kRec = sizeof(sph_task_result);
 constexpr int kMaxStreams = 8;
 constexpr int kMaxBatch = 4096;
+// The completion thread asks about a batch launched less than kSpinNs ago every
+// kAskNs, without sleeping: a sleep, however short it is asked to be, ends some
+// 50 us later, longer than most batches run and than the next one takes to be
+// launched on its stream. Longer batches lose a twentieth to the sleeps at most.
+// A burst of 1127 tasks, median us: sleeping 410, asking 363.
+constexpr int64_t kSpinNs = 1000000, kAskNs = 3000;
 
 size_t al256(size_t b) { return (b + 255) & ~size_t(255); }
 
@@ -190,9 +196,14 @@ struct sph_server {
   // Launch one batch on slot S (mu not held; S is owned by the dispatcher).
   hipError_t launch(Slot& S, sph_status& st) {
     const int nb = (int)S.reqs.size();
+    // the batch's tasks, offsets and items behind one another (each on a
+    // 256-byte boundary, within the room for the largest batch), so that one
+    // copy takes them instead of three
+    const size_t off_at = al256(sizeof(sph_task) * (size_t)nb);
+    const size_t items_at = off_at + al256(sizeof(int32_t) * (size_t)nb);
     sph_task* th = reinterpret_cast<sph_task*>(S.desc_host);
-    int32_t* oh = reinterpret_cast<int32_t*>(S.desc_host + d.tasks_b);
-    int32_t* ih = reinterpret_cast<int32_t*>(S.desc_host + d.tasks_b + d.off_b);
+    int32_t* oh = reinterpret_cast<int32_t*>(S.desc_host + off_at);
+    int32_t* ih = reinterpret_cast<int32_t*>(S.desc_host + items_at);
     size_t o = S.pool_off;
     int nd = 0, ni = 0;
     for (int pass = 0; pass < 2; ++pass) {
@@ -212,19 +223,14 @@ struct sph_server {
       oh[j] = (int32_t)o;
       o += (size_t)S.reqs[j].n_i;
     }
-    hipError_t e = hipMemcpyAsync(S.desc_dev, th, sizeof(sph_task) * nb, hipMemcpyHostToDevice,
-                                  S.stream);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(S.desc_dev + d.tasks_b, oh, sizeof(int32_t) * nb,
-                         hipMemcpyHostToDevice, S.stream);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(S.desc_dev + d.tasks_b + d.off_b, ih, 2 * sizeof(int32_t) * ni,
-                         hipMemcpyHostToDevice, S.stream);
+    hipError_t e = hipMemcpyAsync(S.desc_dev, S.desc_host,
+                                  items_at + 2 * sizeof(int32_t) * (size_t)ni,
+                                  hipMemcpyHostToDevice, S.stream);
     if (e != hipSuccess) return e;
     st = sph_tasks_run(&soa, &prec, &cells, &prm, sph_tile{d.ti, d.k},
                        reinterpret_cast<const sph_task*>(S.desc_dev), nb,
-                       reinterpret_cast<const int32_t*>(S.desc_dev + d.tasks_b),
-                       reinterpret_cast<const int32_t*>(S.desc_dev + d.tasks_b + d.off_b), nd,
+                       reinterpret_cast<const int32_t*>(S.desc_dev + off_at),
+                       reinterpret_cast<const int32_t*>(S.desc_dev + items_at), nd,
                        ni - nd, pool_dev, (int32_t)d.pool_recs, S.stream);
     if (st != SPH_OK) return hipErrorLaunchFailure;
     e = hipMemcpyAsync(S.stage, pool_dev + S.pool_off, kRec * S.pool_n, hipMemcpyDeviceToHost,
@@ -301,7 +307,7 @@ struct sph_server {
     (void)hipSetDevice(device);
     std::unique_lock<std::mutex> lk(mu);
     for (;;) {
-      bool busy = false, progress = false;
+      bool busy = false, progress = false, fresh = false;
       for (int i = 0; i < d.streams; ++i) {
         Slot& S = slots[i];
         if (!S.busy) continue;
@@ -310,7 +316,10 @@ struct sph_server {
         lk.unlock();
         const hipError_t q = hipEventQuery(S.ev);
         lk.lock();
-        if (q == hipErrorNotReady) continue;
+        if (q == hipErrorNotReady) {
+          fresh |= clock_ns() - S.launch_ns < kSpinNs;
+          continue;
+        }
         if (q != hipSuccess) {
           set_fault(std::string("sph_server: batch failed: ") + hipGetErrorString(q));
           S.launched = false;   // never read its records
@@ -349,7 +358,12 @@ struct sph_server {
       }
       if (!progress) {
         lk.unlock();
-        std::this_thread::sleep_for(std::chrono::microseconds(4));
+        if (fresh) {
+          const int64_t t = clock_ns();
+          while (clock_ns() - t < kAskNs) std::this_thread::yield();
+        } else {
+          std::this_thread::sleep_for(std::chrono::microseconds(4));
+        }
         lk.lock();
       }
     }
@@ -472,7 +486,8 @@ sph_status sph_server_submit(sph_server* srv, const sph_request* req, int32_t n,
   if (first_id) *first_id = srv->next_id;
   for (int j = 0; j < n; ++j) {
     Req r{req[j], srv->next_id++, req[j].task.i_end - req[j].task.i_begin};
-    srv->pending.emplace(req[j].arrival_ns, r);
+    // in order of arrival as most are, a request goes behind the last one
+    srv->pending.emplace_hint(srv->pending.end(), req[j].arrival_ns, r);
   }
   srv->submitted += n;
   srv->cv_disp.notify_all();
