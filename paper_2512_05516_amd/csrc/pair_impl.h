@@ -21,7 +21,7 @@
 // partial sums of a particle are combined in a fixed tree: results are
 // bit-identical run to run.
 //
-// What bounds the loops is vector issue (77-80 % of the cycles at 64x1 on the
+// What bounds the loops is vector issue (87 % of the cycles at 64x1 on the
 // 128^3 lattice): the kernel sums take about half of it, the gather and its
 // tables a quarter, tests and lists the rest. Against the version that tested
 // with vector instructions, one candidate per lane and instruction, and kept
@@ -1510,13 +1510,13 @@ __global__ __launch_bounds__(TI* K, kDensityBlocks<TI * K>) void k_density(Src, 
   using Shape = KernelShape<KS>;
   constexpr int NT = TI * K;
   // staged candidates: 2 NT leaves LDS for four waves per SIMD (64x1 on the
-  // 128^3 lattice: 405 us with 256 candidates, 360 with 128)
+  // 128^3 lattice: 431 us with 256 candidates, 382 with 128)
   constexpr int CAP = 2 * NT;
   constexpr int kLimit = batch_limit(K == 1 ? 2 : 3, NT, K);
   // rounds of a gather window (and half the queue): fewer leave more LDS for
   // resident workgroups, more hide more latency (64x1 on the 128^3 lattice,
-  // us: 2 rounds 363, 3 361, 4 357; clustered 32x2, 1.5M: 701, 689, 697; the
-  // wider tiles: 64x4 on 0.88M, 12 per cell: 1 round 328, 2 286, 3 285)
+  // us: 2 rounds 391, 3 382, 4 374; clustered 32x2, 1.5M: 818, 798, 815; the
+  // wider tiles: 64x4 on 0.88M, 64 per cell: 1 round 328, 2 286, 3 285)
   constexpr int KR = NT == 64 ? 3 : 2;
   using Map = TileMap<TI, K>;
   constexpr int RC = CAP / K;     // staged candidates of one lane of the order
@@ -1727,11 +1727,11 @@ __global__ __launch_bounds__(TI* K, kForceBlocks<TI * K>) void k_force(Src, Cell
                                                                  float s32, Items items) {
   using Shape = KernelShape<KS>;
   constexpr int NT = TI * K;
-  constexpr int CAP = 2 * NT;     // whole groups
+  constexpr int CAP = 2 * NT;     // staged candidates
   constexpr int kLimit = batch_limit(2, NT, K);
   // rounds of a gather window: two keep the workgroup's LDS within 1/12 of
-  // the CU's (64x1 on the 128^3 lattice, us: 2 rounds 564, 3 591; 64x4 on
-  // 0.88M: 1 round 489, 2 411, 3 414)
+  // the CU's (64x1 on the 128^3 lattice, us: 2 rounds 606, 3 626; 32x2
+  // 678, 719; 64x4 on 0.88M: 1 round 489, 2 411, 3 414)
   constexpr int KR = 2;
   using Map = TileMap<TI, K>;
   constexpr int RC = CAP / K;     // staged candidates of one lane of the order
