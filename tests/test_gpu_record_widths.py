@@ -101,3 +101,36 @@ def test_record_widths(sph, n, lay):
             else:
                 want[k][perm] = new["UK" if k == "u" else SOA[k]].numpy()
         assert np.array_equal(pipe.aos.cpu().numpy(), buf), view
+
+
+@pytest.mark.parametrize("lay", range(len(LAYOUTS)))
+@pytest.mark.parametrize("n", [1, 257])
+def test_kick_of_records(sph, n, lay):
+    """The records' kick (FP32, FP64 and mixed fields) is the slots' kick
+    written back, to the byte, and counts the same moves."""
+    import torch
+    from paper_2512_05516_amd.pipeline import Pipeline
+    dt = LAYOUTS[lay]
+    rng = np.random.default_rng(n + lay)
+    raw = rng.integers(0, 256, n * dt.itemsize, dtype=np.uint8)
+    rec = raw.view(dt)
+    rec["x"] = rng.uniform(0, 1, (n, 3))
+    for k in ("v", "a", "m", "h", "u", "du"):
+        rec[k] = rng.normal(0, 1, rec[k].shape).astype(np.float32)
+    rec["h"] = 0.01
+    out = []
+    for aos in (False, True):
+        pipe = Pipeline(rec, 3)
+        pipe.bin()
+        if aos:
+            pipe.kick_drift_aos(0.05, 0.05)
+        else:
+            pipe.convert("full")
+            perm = pipe.cells.perm[:n].cpu().numpy()
+            for c, ax in enumerate("XYZ"):
+                pipe.soa["A_" + ax].copy_(torch.from_numpy(rec["a"][perm, c].astype(np.float32)))
+            pipe.soa["DU"].copy_(torch.from_numpy(rec["du"][perm].astype(np.float32)))
+            pipe.kick_drift(0.05, 0.05)
+            pipe.writeback("kick")
+        out.append((pipe.aos.cpu().numpy(), pipe.moved.item()))
+    assert np.array_equal(out[0][0], out[1][0]) and out[0][1] == out[1][1]
