@@ -1,0 +1,70 @@
+"""The dynamic schedule's queues: every item is taken exactly once, with fewer
+items than queues, than workgroups, and many more, and the launch's end, when
+all workgroups come by all queues, does not outlast the work."""
+import numpy as np
+import pytest
+
+from paper_2512_05516_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+OUT = ("RHO", "WCOUNT", "RHO_DH", "F", "P", "C", "NNGB", "A_X", "A_Y", "A_Z", "DU", "VSIG", "NFORCE")
+
+
+@pytest.fixture(scope="module")
+def sph():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2512_05516_amd import sphmi
+    sphmi.lib()
+    return sphmi
+
+
+def _pipe(sph, n, n_c, tile, sched):
+    from paper_2512_05516_amd.pipeline import Pipeline
+    rng = np.random.default_rng(n + n_c)
+    x = rng.uniform(0, 1, (n, 3)) ** (2 if n_c < 10 else 1)      # a small set's cells: uneven
+    h = rng.uniform(0.4, 0.9, n) / (n_c * sph.GAMMA_K[0])
+    ps = inputs.ParticleSet(x, rng.normal(0, 0.1, (n, 3)), rng.uniform(0.5, 1.5, n) / n, h,
+                            rng.uniform(0.5, 1.5, n))
+    pipe = Pipeline(inputs.pack_aos(ps, "f32"), n_c, til=sph.tile(*tile), sched=sched)
+    pipe.bin()
+    pipe.convert("full")
+    return pipe
+
+
+@pytest.mark.parametrize("n,n_c,tile", [(3, 3, (64, 1)), (40, 3, (16, 4)), (700, 4, (16, 16)),
+                                        (5000, 5, (64, 4)), (64000, 10, (128, 2)),
+                                        (60000, 20, (32, 2))])
+def test_every_item_once(sph, n, n_c, tile):
+    import torch
+    grid, dyn = (_pipe(sph, n, n_c, tile, s) for s in ("grid", "dynamic"))
+    for p in (grid, dyn, dyn, dyn):
+        for k in OUT:
+            p.soa[k].fill_(-1)
+        p.density()
+        p.force()
+        for k in OUT:
+            assert torch.equal(p.soa[k].view(torch.int32), grid.soa[k].view(torch.int32)), k
+
+
+def test_the_end_of_a_launch(sph):
+    """Against one workgroup per item on the same lists. Bar: 5 times (an
+    atomic for every try took 21 and 8.7 times; now 2.4 and 1.8)."""
+    import torch
+    pipes = [_pipe(sph, 64000, 10, (128, 2), s) for s in ("grid", "dynamic")]
+    t = {}
+    for loop in ("density", "force"):
+        for rep in range(8):
+            for i, p in enumerate(pipes):
+                e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+                e0.record()
+                for _ in range(5):
+                    getattr(p, loop)()
+                e1.record()
+                torch.cuda.synchronize()
+                t.setdefault((loop, i), []).append(e0.elapsed_time(e1))
+    for loop in ("density", "force"):
+        grid, dyn = (np.median(t[loop, i][2:]) for i in (0, 1))
+        assert dyn <= 5 * grid, (loop, grid, dyn)
