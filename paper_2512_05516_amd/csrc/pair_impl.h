@@ -1233,11 +1233,21 @@ __device__ __forceinline__ void test_and_consume(uint8_t* wl, int ntile, Masks m
     }
     return tot;
   };
+  // the lowest and the highest bit of m in turn, which become entries from the
+  // front and from the back of m's part of the list: two chains that do not wait
+  // for each other (the last of an odd number is written twice)
   auto append = [&](unsigned m, uint8_t*& le, unsigned base) {
+    const int k = NL * __popc(m);
+    uint8_t *lo = le, *hi = le + k - NL;
+    le += k;
     while (m) {
-      *le = (uint8_t)((unsigned)__builtin_ctz(m) + base);
-      le += NL;
+      const unsigned top = __builtin_clz(m);
+      *lo = (uint8_t)((unsigned)__builtin_ctz(m) + base);
+      *hi = (uint8_t)(31u - top + base);
+      lo += NL;
+      hi -= NL;
       m &= m - 1;
+      m &= ~(0x80000000u >> top);
     }
   };
   auto sums = [&] {      // the list of this thread's sum was counted by another lane
