@@ -2063,14 +2063,18 @@ __global__ __launch_bounds__(TI* K, kForceBlocks<TI * K>) void k_force(Src, Cell
       atomicAdd(cd.tally, (unsigned long long)(c1 - c0) * (unsigned long long)gs.kept);
       atomicAdd(cd.tally + 1, (unsigned long long)gathered);
     }
+    // over the threads of a sum as within one: the same integer maximum, which
+    // keeps the NaN of a neighbour's sound speed however the chunk is laid out
+    int vsi = __float_as_int(vsig);
     if (F >= 2) {
-      vsig = fmaxf(vsig, __shfl_xor(vsig, 1));
+      vsi = max(vsi, __shfl_xor(vsi, 1));
       nf += __shfl_xor(nf, 1);
     }
     if (F == 4) {
-      vsig = fmaxf(vsig, __shfl_xor(vsig, 2));
+      vsi = max(vsi, __shfl_xor(vsi, 2));
       nf += __shfl_xor(nf, 2);
     }
+    vsig = __int_as_float(vsi);
     float sum[6] = {ax, ay, az, du, vsig, __int_as_float(nf)};
     over_lanes<TI, K>(kk, gi, vi && f == 0, sum, reinterpret_cast<float*>(cp),
                       [](int k, float a, float b) {
