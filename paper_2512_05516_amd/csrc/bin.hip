@@ -215,7 +215,7 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
     all = hist[tid];
   }
   for (int e = lane; e < NB; e += 64) wcnt[wave][e] = 0;
-  __builtin_amdgcn_wave_barrier();
+  wave_sync();
   int at[kRounds];            // keys of the same digit before it in the wave
 #pragma unroll
   for (int r = 0; r < kRounds; ++r) {
@@ -230,9 +230,9 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
     const int rank = __popcll(m & lanemask_lt());
     const int before = wcnt[wave][d];
     at[r] = before + rank;
-    __builtin_amdgcn_wave_barrier();     // every lane has read its count
+    wave_sync();     // every lane has read its count
     if (valid && rank == 0) wcnt[wave][d] = (uint16_t)(before + __popcll(m));
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
   }
   __syncthreads();
   int cnt = 0;

@@ -1277,8 +1277,12 @@ __device__ __forceinline__ void test_and_consume(uint8_t* wl, int ntile, Masks m
       m &= ~(0x80000000u >> top);
     }
   };
-  auto sums = [&] {      // the list of this thread's sum was counted by another lane
+  // the list of this thread's sum was counted, and may have been written, by
+  // other lanes, which write the next one when all have read this
+  auto sums = [&] {
+    wave_sync();
     consume(L == 1 ? n : __shfl(n, (lane / (F * PB)) * F * PB + (lane / F) % PB));
+    wave_sync();
     n = 0;
   };
   for (int G = 0; 8 * G < ntile; ++G) {

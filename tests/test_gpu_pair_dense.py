@@ -61,3 +61,20 @@ def test_all_pairs_accepted(sph, orc, ti, k, n, own):
     assert max_rel(got["vsig"], f["vsig"]) <= 1e-5
     for q in ("a", "du"):
         assert rel_rmse(got[q], f[q]) <= 1e-5, q
+
+
+@pytest.mark.parametrize("n", [3, 16, 24, 32])
+@pytest.mark.parametrize("ti,k", [(64, 1), (64, 2), (32, 2), (16, 4)])
+def test_lists_that_lanes_share(sph, orc, ti, k, n):
+    """Chunks of few particles, whose lists are written by up to four lanes and
+    read by others: the same bits on every launch."""
+    import torch
+    ps = _dense(orc, 10 * n, n)
+    pipe = run_gpu(ps, N_C, "f32", til=sph.tile(ti, k), prm=sph.params(gradh=False))
+    out = ("RHO", "WCOUNT", "RHO_DH", "NNGB", "A_X", "A_Y", "A_Z", "DU", "VSIG", "NFORCE")
+    first = {q: pipe.soa[q].clone() for q in out}
+    for _ in range(20):
+        pipe.density()
+        pipe.force()
+        for q in out:
+            assert torch.equal(pipe.soa[q].view(torch.int32), first[q].view(torch.int32)), q
