@@ -307,12 +307,13 @@ struct sph_server {
     (void)hipSetDevice(device);
     std::unique_lock<std::mutex> lk(mu);
     for (;;) {
-      bool busy = false, progress = false, fresh = false;
+      bool busy = false, waits = false, progress = false, fresh = false;
       for (int i = 0; i < d.streams; ++i) {
         Slot& S = slots[i];
         if (!S.busy) continue;
         busy = true;
         if (!S.launched) continue;
+        waits = true;
         lk.unlock();
         const hipError_t q = hipEventQuery(S.ev);
         lk.lock();
@@ -353,6 +354,10 @@ struct sph_server {
         if (!others) break;
       } else if (!busy) {
         if (stop) break;
+        cv_comp.wait(lk);
+        continue;
+      }
+      if (!waits && busy && fault == SPH_OK) {   // being launched: the dispatcher notifies
         cv_comp.wait(lk);
         continue;
       }
