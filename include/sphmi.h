@@ -620,6 +620,9 @@ sph_status sph_tasks_run(const sph_soa *soa, const sph_precision *prec, const sp
 /* the requests' host buffers, frees its pool memory and time-stamps    */
 /* it. A task's records depend only on the task and the resident state, */
 /* never on the batch it ran in.                                        */
+/* Both threads sleep while they wait. The completion thread looks at   */
+/* the batches in flight every sixteenth of their time (4 to 50 us),    */
+/* which takes it up to a third of a core while batches run.            */
 /* ------------------------------------------------------------------ */
 typedef struct sph_server sph_server;   /* opaque */
 
