@@ -1,6 +1,8 @@
 // Cell binning: FP64 cell ids, a stable LSD radix sort by cell id, and the
 // CSR cell_start table. The order is stable by (cell id, input index), so
 // the permutation is identical on every run and on every device.
+#include <algorithm>
+
 #include "sph_device.h"
 
 namespace sph {
@@ -362,13 +364,13 @@ struct BinWs {
   float* hin;   // h per input slot
 };
 
-// The workspace holds counts for tiles of kWsTile keys, and its size a few
-// words for each kWsScan of those; both are more than a sort uses.
-constexpr int kWsTile = 2048, kWsScan = 4096;
-static_assert(kWsTile <= kTile, "counts of a tile fit");
+// Workspace: four arrays of keys and values, the tiles' digit counts, h
+size_t al(size_t b) { return (b + 255) & ~size_t(255); }
+size_t hist_bytes(int n) {
+  return al(sizeof(int32_t) * (size_t)kMaxBuckets * (size_t)std::max(cdiv(n, kTile), 1));
+}
 
 BinWs carve(void* ws, int n) {
-  auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
   char* p = static_cast<char*>(ws);
   BinWs w;
   size_t nb = al(sizeof(int32_t) * (size_t)(n > 0 ? n : 1));
@@ -376,9 +378,7 @@ BinWs carve(void* ws, int n) {
   w.va = reinterpret_cast<int32_t*>(p); p += nb;
   w.kb = reinterpret_cast<int32_t*>(p); p += nb;
   w.vb = reinterpret_cast<int32_t*>(p); p += nb;
-  const int nblk = cdiv(n, kWsTile);
-  size_t hl = (size_t)kMaxBuckets * (size_t)(nblk > 0 ? nblk : 1);
-  w.hist = reinterpret_cast<int32_t*>(p); p += al(sizeof(int32_t) * hl);
+  w.hist = reinterpret_cast<int32_t*>(p); p += hist_bytes(n);
   w.hin = reinterpret_cast<float*>(p);
   return w;
 }
@@ -401,11 +401,7 @@ hipError_t radix_pass(const int32_t* ks, const int32_t* vs, int32_t* kd, int32_t
 size_t bin_workspace_bytes(int n, int n_c, int sub_bits) {
   (void)n_c;
   (void)sub_bits;
-  auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
-  int nblk = cdiv(n, kWsTile);
-  size_t hl = (size_t)kMaxBuckets * (size_t)(nblk > 0 ? nblk : 1);
-  return 5 * al(sizeof(int32_t) * (size_t)(n > 0 ? n : 1)) + al(sizeof(int32_t) * hl) +
-         al(sizeof(int32_t) * ((size_t)cdiv((int64_t)hl, kWsScan) + 1));
+  return 5 * al(sizeof(int32_t) * (size_t)(n > 0 ? n : 1)) + hist_bytes(n);
 }
 
 hipError_t launch_bin(const void* aos, const AosLayout& L, const CellsDev& c, int32_t* cell_start,

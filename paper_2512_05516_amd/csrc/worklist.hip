@@ -12,7 +12,7 @@
 // Buffer layout: [0, kWorkHeader) queue counters[8] and meta (item count,
 // range boundaries[9]); then the prefixes of the items and of the costs of
 // the cells in brick order ([C + 1] each, see k_wl_count) and the items (int2:
-// cell, first slot), after a gap that is part of the buffer's size.
+// cell, first slot).
 //
 // Two launches: the lists are short (a few us of work), so what a build costs
 // is its launches. With separate scans of items and costs and a kernel for the
@@ -38,8 +38,6 @@ struct WlLayout {
 };
 
 size_t al256(size_t b) { return (b + 255) & ~size_t(255); }
-// unused words between the prefixes and the items
-size_t gap_bytes(int C) { return al256(sizeof(int32_t) * ((size_t)cdiv(C + 1, 4096) + 1)); }
 
 WlLayout wl_layout(void* buf, int C) {
   char* p = static_cast<char*>(buf) + kWorkHeader;
@@ -48,7 +46,6 @@ WlLayout wl_layout(void* buf, int C) {
   p += al256(sizeof(int32_t) * ((size_t)C + 1));
   L.cost = reinterpret_cast<int32_t*>(p);
   p += al256(sizeof(int32_t) * ((size_t)C + 1));
-  p += gap_bytes(C);
   L.items = reinterpret_cast<int2*>(p);
   return L;
 }
@@ -293,8 +290,7 @@ int worklist_capacity(int n, int n_c, int ti) {
 size_t worklist_bytes(int n, int n_c, int ti) {
   const int C = n_c * n_c * n_c;
   const int cap = worklist_capacity(n, n_c, ti);
-  return kWorkHeader + 2 * al256(sizeof(int32_t) * ((size_t)C + 1)) +
-         gap_bytes(C) + sizeof(int2) * (size_t)cap;
+  return kWorkHeader + 2 * al256(sizeof(int32_t) * ((size_t)C + 1)) + sizeof(int2) * (size_t)cap;
 }
 
 hipError_t launch_worklist(const CellsDev& c, const WorkDev& w, hipStream_t s) {
