@@ -1229,12 +1229,19 @@ constexpr int kListWave = 64 * 32;
 // gives the accepted candidates of group G; they are appended to the lists in
 // order, and `consume(n)` runs phase B over the lists (n: entries of the list
 // of this thread's sum), at the end and, where a list would overflow with the
-// next group, before. A group too dense for empty lists is taken 32 candidates at
-// a time; with DIRECT, where every lane has its own list, `bits(m, base)` then
-// runs phase B over the bits of the word itself, in the same order: the list
-// would hold no more than that word, and making it costs a third of using it
-// (force, 26617 clustered particles, 64x1, merged: 324 -> 295 us).
-template <int PB, int F, int KC, int RC, bool DIRECT, class Masks, class Consume, class Bits>
+// next group, before. A group too dense for the lists is taken 32 candidates at a
+// time. PARTS says how:
+//   kFill: the lists take words until one does not fit (the density loop, whose
+//   sums per entry cost no more than the entry: 110592 particles, 64x2, 39.5 ->
+//   37.5 us; clustered 1.5M, 64x1, 738 -> 730);
+//   kDirect: where every lane has its own list, `bits(m, base)` runs phase B over
+//   the bits of the word itself, in the same order, and there is no list to make
+//   (force, 26617 clustered particles, 64x1, merged: 324 -> 295 us; filled lists
+//   302);
+//   kEach: a list per word (force, several threads per sum: as fast as kFill and
+//   smaller).
+enum : int { kFill, kDirect, kEach };
+template <int PB, int F, int KC, int RC, int PARTS, class Masks, class Consume, class Bits>
 __device__ __forceinline__ void test_and_consume(uint8_t* wl, int ntile, Masks masks,
                                                  Consume consume, Bits bits) {
   constexpr int NB = PB / 16, L = 64 / PB, NL = 64 / F, LP = kListWave / NL, RG = 4 / KC;
@@ -1298,6 +1305,36 @@ __device__ __forceinline__ void test_and_consume(uint8_t* wl, int ntile, Masks m
       return (unsigned)((rg / RG) * RC + 32 * RG * G + 4 * nt * (rg % RG));
     };
     const bool last = 8 * G + 8 >= ntile;
+    if constexpr (PARTS == kFill) {
+      int row = RG;                 // row groups of a group that is taken in parts
+      if (__any(n + tot > LP)) {
+        row = 0;
+      } else {
+        uint8_t* le = pl + (n + pre) * NL;
+#pragma unroll
+        for (int j = 0; j < NB; ++j) append(w[j], le, base(j));
+        n += tot;
+      }
+      for (;; ++row) {              // one call site of the sums: they are large code
+        unsigned m = 0u, b0 = 0u;
+        int t = 0, p = 0;
+        if (row < RG) {
+#pragma unroll
+          for (int j = 0; j < NB; ++j) {
+            const bool mine = (tr * NB + j) % RG == row;
+            m = mine ? w[j] : m;
+            b0 = mine ? base(j) : b0;
+          }
+          t = share(__popc(m), p);
+        }
+        if (row < RG ? __any(n + t > LP) : last) sums();
+        if (row == RG) break;
+        uint8_t* le = pl + (n + p) * NL;
+        append(m, le, b0);
+        n += t;
+      }
+      continue;
+    }
     for (int row = -1;;) {          // row groups of a group that is taken in parts
       if (row < 0 && !__any(n + tot > LP)) {
         uint8_t* le = pl + (n + pre) * NL;
@@ -1315,7 +1352,7 @@ __device__ __forceinline__ void test_and_consume(uint8_t* wl, int ntile, Masks m
           m = mine ? w[j] : m;
           b0 = mine ? base(j) : b0;
         }
-        if constexpr (DIRECT && L == 1) {
+        if constexpr (PARTS == kDirect && L == 1) {
           bits(m, b0);
           if (++row == RG) break;
           continue;
@@ -1693,7 +1730,7 @@ __global__ __launch_bounds__(TI* K, kDensityBlocks<TI * K>) void k_density(Src, 
         const Prefilter<PB, F> pf(usable ? m2x : 0.0f, usable ? m2y : 0.0f, usable ? m2z : 0.0f);
         float nc[NB];
         pf.per_block(negc, nc);
-        test_and_consume<PB, F, Map::KC, RC, false>(
+        test_and_consume<PB, F, Map::KC, RC, kFill>(
             wl, ntile,
             [&](int G, int nt, unsigned(&w)[NB]) {
               group_masks<NB, Map::KC, RC, false>(cw, nullptr, G, nt, pf.b, nc, w);
@@ -2013,7 +2050,7 @@ __global__ __launch_bounds__(TI* K, kForceBlocks<TI * K>) void k_force(Src, Cell
         const Prefilter<PB, F> pf(usable ? m2x : 0.0f, usable ? m2y : 0.0f, usable ? m2z : 0.0f);
         float nc[NB];
         pf.per_block(negc, nc);
-        test_and_consume<PB, F, Map::KC, RC, F == 1>(
+        test_and_consume<PB, F, Map::KC, RC, F == 1 ? kDirect : kEach>(
             wl, ntile,
             [&](int G, int nt, unsigned(&w)[NB]) {
               group_masks<NB, Map::KC, RC, false>(pw, nullptr, G, nt, pf.b, nc, w);
