@@ -1843,7 +1843,7 @@ __global__ __launch_bounds__(TI* K, kForceBlocks<TI * K>) void k_force(Src, Cell
   constexpr int kLimit = batch_limit(2, NT, K);
   // rounds of a gather window: two keep the workgroup's LDS within 1/12 of
   // the CU's (64x1 on the 128^3 lattice, us: 2 rounds 606, 3 626; 32x2
-  // 678, 719; 64x4 on 0.88M: 1 round 489, 2 411, 3 414)
+  // 678, 719; 64x4 on 0.88M: 1 round 489, 2 411, 3 414).
   constexpr int KR = 2;
   using Map = TileMap<TI, K>;
   constexpr int RC = CAP / K;     // staged candidates of one lane of the order
@@ -2045,6 +2045,54 @@ __global__ __launch_bounds__(TI* K, kForceBlocks<TI * K>) void k_force(Src, Cell
           }
         }
       };
+      // two accepted candidates of one lane, t1 only where `two`: the terms of both
+      // are computed side by side and added in order. Where few waves run, the loop
+      // over a dense word is a chain of instructions that wait for each other (force,
+      // 26617 clustered particles, 64x1, merged: 295 -> 282 us; 34295, 32x8: 338 ->
+      // 318).
+      auto pair2 = [&](int t0, int t1, bool two) {
+        const int t[2] = {t0, t1};
+        float4 q0[2], q1[2], q2[2];
+        float h2j[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          q0[u] = pw[t[u]];
+          h2j[u] = hw[t[u]];
+          q1[u] = vw[t[u]];
+          q2[u] = sw[t[u]];
+        }
+        float kc[2], ke[2], ex[2], ey[2], ez[2], w[2], vs[2];
+        bool skip[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          float dx, dy, dz;
+          const float r2 = dist2_m2(m2x, m2y, m2z, q0[u].x, q0[u].y, q0[u].z, dx, dy, dz);
+          skip[u] = !((r2 < H2i) | (r2 < h2j[u])) | (t[u] == tself) | (u == 1 && !two);
+          const float r = fast_sqrt(r2);
+          const float rinv = r2 > 0.0f ? fast_rcp(r) : 0.0f;
+          ex[u] = dx * rinv, ey[u] = dy * rinv, ez[u] = dz * rinv;
+          const float gi_ = Shape::dw(r * Hinvi) * Hinv4i;
+          const float hj2 = q2[u].x * q2[u].x;
+          const float gj_ = Shape::dw(r * q2[u].x) * (hj2 * hj2);
+          w[u] = (vxi - q1[u].x) * ex[u] + (vyi - q1[u].y) * ey[u] + (vzi - q1[u].z) * ez[u];
+          const float mu = fminf(w[u], 0.0f);
+          vs[u] = ci + q2[u].z - beta * mu;
+          const float visc = -alpha * vs[u] * mu * fast_rcp(rhoi + q2[u].w);
+          const float gbar = 0.5f * (gi_ + gj_);
+          kc[u] = q1[u].w * (Ai * gi_ + q2[u].y * gj_ + visc * gbar);
+          ke[u] = q1[u].w * (Ai * gi_ + 0.5f * visc * gbar);
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          if (skip[u]) continue;
+          ax = fmaf(-kc[u], ex[u], ax);
+          ay = fmaf(-kc[u], ey[u], ay);
+          az = fmaf(-kc[u], ez[u], az);
+          du = fmaf(ke[u], w[u], du);
+          vsig = __int_as_float(max(__float_as_int(vsig), __float_as_int(vs[u])));
+          ++nf;
+        }
+      };
       with_block<Map::Q>(PB, [&](auto pb, auto fc) {
         constexpr int PB = decltype(pb)::value, F = decltype(fc)::value, NB = PB / 16;
         const Prefilter<PB, F> pf(usable ? m2x : 0.0f, usable ? m2y : 0.0f, usable ? m2z : 0.0f);
@@ -2073,7 +2121,13 @@ __global__ __launch_bounds__(TI* K, kForceBlocks<TI * K>) void k_force(Src, Cell
               }
             },
             [&](unsigned m, unsigned b0) {
-              for (; m; m &= m - 1) pair(fc, (int)(b0 + __builtin_ctz(m)), true, [] {});
+              while (m) {      // two at a time; the last of an odd number twice
+                const int t0 = (int)(b0 + __builtin_ctz(m));
+                m &= m - 1;
+                const int t1 = m ? (int)(b0 + __builtin_ctz(m)) : t0;
+                pair2(t0, t1, m != 0u);
+                m &= m - 1;
+              }
             });
       });
     };
