@@ -1843,8 +1843,11 @@ __global__ __launch_bounds__(TI* K, kForceBlocks<TI * K>) void k_force(Src, Cell
   constexpr int kLimit = batch_limit(2, NT, K);
   // rounds of a gather window: two keep the workgroup's LDS within 1/12 of
   // the CU's (64x1 on the 128^3 lattice, us: 2 rounds 606, 3 626; 32x2
-  // 678, 719; 64x4 on 0.88M: 1 round 489, 2 411, 3 414).
-  constexpr int KR = 2;
+  // 678, 719; 64x4 on 0.88M: 1 round 489, 2 411, 3 414). Workgroups of two waves
+  // have room for four, and small launches wait for fewer windows (64x2: 4096
+  // particles 34.7 -> 31.0, 9001 clustered 79 -> 76, 120001 clustered 191 -> 181);
+  // records' positions, three FP64 values each, would take too many registers.
+  constexpr int KR = NT == 128 && std::is_same_v<typename Src::Origin, NoOrigin> ? 4 : 2;
   using Map = TileMap<TI, K>;
   constexpr int RC = CAP / K;     // staged candidates of one lane of the order
   static_assert(Map::KC * RC <= 256, "list entries are bytes");
