@@ -1450,8 +1450,8 @@ __device__ __forceinline__ float dist2_m2(float m2x, float m2y, float m2z, float
 // cell, cell + 1, ... of one brick row, at most TI of them.
 // The chunk callback takes (cell, m, c0, c1, only_q, out, obase): slots
 // [c0, c1) of the m cells from `cell` along x, the neighbour cell index q
-// (0..26) the j particles are restricted to (-1: all of them; only with
-// m = 1), and the task result records (out == nullptr: the full loop's
+// (0..26) the j particles are restricted to (-1: all of them, -2: none; else
+// only with m = 1), and the task result records (out == nullptr: the full loop's
 // outputs) with slot i's record at out[obase + i].
 // Position of slot i of a chunk over the m cells from `cell` along x,
 // relative to `cell`: the stored offset in i's own cell, shifted by that
@@ -1912,7 +1912,7 @@ __global__ __launch_bounds__(TI* K, kForceBlocks<TI * K>) void k_force(Src, Cell
     // max: t < max(H_i^2, Hn^2) - |p|^2 + M, with Hn bounding every H_j of
     // the 27 cells, accepts a superset of the pairs at a few extra entries,
     // and the consume phase applies the exact test to each of them.
-    const float hn = uniform(only_q == -1 ? T.hbmax : T.hb[only_q]);
+    const float hn = uniform(only_q < 0 ? T.hbmax : T.hb[only_q]);
     const float hn2 = hn * hn;
     const bool flat = hn2 <= kFlatRatio * bx.h2max;   // uniform over the block
     const float nc0 = pp - mrg - (flat ? fmaxf(H2i, hn2) : H2i);
