@@ -26,13 +26,18 @@
 // tables a quarter, tests and lists the rest. Against the version that tested
 // with vector instructions, one candidate per lane and instruction, and kept
 // gather state in registers across the pair phase (us, density / force):
-//   128^3 lattice, 64 per cell   64x1  417 / 621 -> 376 / 604
-//                                32x2  443 / 777 -> 426 / 676
-//   0.88M lattice, 12 per cell   64x1  580 / 974 -> 347 / 544
-//                                16x4  359 / 632 -> 331 / 530
-//   clustered 1.5M, uneven       64x1  1482 / 2587 -> 887 / 1398
-//                                32x2  990 / 1733 -> 802 / 1269
-// A cell that fills its tile gains least: its time is the kernel sums'.
+//   128^3 lattice, 64 per cell   64x1  358 / 558 -> 342 / 539
+//                                32x2  386 / 727 -> 388 / 668
+//   0.88M lattice, 12 per cell   64x1  539 / 957 -> 315 / 516
+//                                16x4  329 / 610 -> 306 / 510
+//   clustered 1.5M, uneven       64x1  1286 / 2327 -> 728 / 1220
+//                                32x2  883 / 1628 -> 714 / 1184
+//   clustered 18170, 64x2              52 / 92   ->  50 / 100
+// A cell that fills its tile gains least: its time is the kernel sums'. Launches
+// of fewer chunks than the chip holds take the time of their longest chunk, most
+// of it the sums over dense groups in one wave; there the queue's second round of
+// loads and its barriers show, and the last line is the one kind of set found
+// (a few tens of thousands of particles, uneven, 64x2) that lost time.
 //
 // The loaders (SoA views in compile-time or run-time storage formats, or
 // AoS records) are the only difference between the SoA kernels and the
@@ -1608,8 +1613,9 @@ struct TaskItems {
 // --------------------------------------------------------------------------
 // The second launch bound: the compiler reads it as waves per SIMD =
 // blocks x ceil(waves per block / 4). Four waves per SIMD (at most 128
-// VGPRs, a few spilled) for every density tile, three (168 VGPRs) for every
-// force tile.
+// VGPRs; tiles of 64 particles spill one to three) for every density tile,
+// three (168 VGPRs; 64x2 spills three, on records the 64-particle tiles up to 17)
+// for every force tile.
 template <int NT>
 constexpr int kDensityBlocks = 4;
 template <int NT>
