@@ -1512,6 +1512,10 @@ struct LoopItems {
     for (int it = lo + (int)(blockIdx.x / kQueues); it < hi; it += nl) item(it);
     return;
   }
+  // more workgroups than items (small sets, filtered lists): the others would
+  // only stand in line at the queues (4096 particles, 128x2, density / force us: 572
+  // / 146, now 22 / 25)
+  if ((int)blockIdx.x >= (total + kQueues - 1) / kQueues * kQueues) return;
   __shared__ int s_item;
   int qi = 0;   // thread 0: queue it takes items from, counted from its own
   // Item of the next queue that holds one. The queues are looked at first, all
@@ -1519,7 +1523,7 @@ struct LoopItems {
   // empty stays so): at the end of a launch every workgroup comes by every
   // queue, and atomics on all of them, served one after the other, took longer
   // than the work (64000 particles, 128x2, density / force us: 534 / 365, now
-  // 60 / 74; 512000: 808 / 731, now 364 / 425).
+  // 52 / 74; 512000: 808 / 731, now 366 / 427).
   auto grab = [&]() {
     unsigned open = 0u;
 #pragma unroll
@@ -1538,7 +1542,15 @@ struct LoopItems {
     qi = kQueues;
     return -1;
   };
-  if (threadIdx.x == 0) s_item = grab();
+  if (threadIdx.x == 0) {
+    const int first = atomicAdd(&wk.counters[x], 1);
+    if (first < min(wk.meta[2 + x], total)) {
+      s_item = first;
+    } else {
+      qi = 1;
+      s_item = grab();
+    }
+  }
   __syncthreads();
   int it = __builtin_amdgcn_readfirstlane(s_item);
   while (it >= 0) {

@@ -21,10 +21,10 @@ def sph():
     return sphmi
 
 
-def _pipe(sph, n, n_c, tile, sched):
+def _pipe(sph, n, n_c, tile, sched, even=False):
     from paper_2512_05516_amd.pipeline import Pipeline
     rng = np.random.default_rng(n + n_c)
-    x = rng.uniform(0, 1, (n, 3)) ** (2 if n_c < 10 else 1)      # a small set's cells: uneven
+    x = rng.uniform(0, 1, (n, 3)) ** (1 if even or n_c >= 10 else 2)    # a small set's cells: uneven
     h = rng.uniform(0.4, 0.9, n) / (n_c * sph.GAMMA_K[0])
     ps = inputs.ParticleSet(x, rng.normal(0, 0.1, (n, 3)), rng.uniform(0.5, 1.5, n) / n, h,
                             rng.uniform(0.5, 1.5, n))
@@ -61,6 +61,28 @@ def test_the_end_of_a_launch(sph):
                 e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
                 e0.record()
                 for _ in range(5):
+                    getattr(p, loop)()
+                e1.record()
+                torch.cuda.synchronize()
+                t.setdefault((loop, i), []).append(e0.elapsed_time(e1))
+    for loop in ("density", "force"):
+        grid, dyn = (np.median(t[loop, i][2:]) for i in (0, 1))
+        assert dyn <= 5 * grid, (loop, grid, dyn)
+
+
+@pytest.mark.parametrize("n,n_c", [(4096, 4), (8000, 5), (13824, 6)])
+def test_fewer_items_than_workgroups(sph, n, n_c):
+    """As above on sets of fewer items than workgroups stay resident. Bar: 5
+    times (all workgroups at the queues: 15 to 33; now 1.4)."""
+    import torch
+    pipes = [_pipe(sph, n, n_c, (128, 2), s, even=True) for s in ("grid", "dynamic")]
+    t = {}
+    for loop in ("density", "force"):
+        for rep in range(8):
+            for i, p in enumerate(pipes):
+                e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+                e0.record()
+                for _ in range(20):
                     getattr(p, loop)()
                 e1.record()
                 torch.cuda.synchronize()
