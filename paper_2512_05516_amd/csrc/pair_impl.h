@@ -1000,7 +1000,7 @@ __device__ __forceinline__ void for_lds_batches(int n, bool exact, Fill fill, Pa
   static_assert(CAP % kStep == 0 && CAP % K == 0, "whole steps");
   __syncthreads();     // the queue
   if constexpr (EXACT) {
-    // ceil(n / parts), parts = 1 to 4, through v_rcp (1 ulp): exact, (n + parts - 1)
+    // ceil(n / parts), parts = 1 to 5, through v_rcp (1 ulp): exact, (n + parts - 1)
     // / parts + 2^-10 lies at least 2^-10 from an integer
     const int parts = (n + CAP - 1) / CAP;
     const int even = __builtin_amdgcn_readfirstlane(
