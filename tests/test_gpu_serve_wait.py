@@ -25,8 +25,11 @@ def _cpu():
     """CPU time in ns of each of the process's threads."""
     out = {}
     for t in glob.glob("/proc/self/task/*"):
-        with open(os.path.join(t, "schedstat")) as f:
-            out[os.path.basename(t)] = int(f.read().split()[0])
+        try:
+            with open(os.path.join(t, "schedstat")) as f:
+                out[os.path.basename(t)] = int(f.read().split()[0])
+        except (FileNotFoundError, ProcessLookupError):      # a thread that ended meanwhile
+            pass
     return out
 
 
